@@ -195,6 +195,20 @@ __device__ __forceinline__ void block_sync_vm()
     __syncthreads();
 }
 
+// Store v in *flag for readers on other chiplets, everything this workgroup
+// stored before its last block_sync_vm() being visible to a reader that sees
+// it and takes an acquire fence.  The release fence writes this chiplet's L2
+// back, which completes later than it issues: the wait behind it is written
+// out because the compiler drops its own when it counts no other memory
+// operation in flight (ROCm 7.2; the flag then overtook the write-back, and
+// a reader could take stale token sets).  One thread calls it.
+__device__ __forceinline__ void publish_release(int32_t *flag, int32_t v)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ void set_status(UttState &st, int code)
 {
     atomicCAS(&st.status, 0, code);

@@ -1093,7 +1093,7 @@ __global__ __launch_bounds__(kT) void search_kernel(Params p)
     const int tid = threadIdx.x;
     UttState &st = p.st[u];
     if (st.status != 0) {
-        if (p.pub_k && tid == 0) __hip_atomic_store(p.prog + u, -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (p.pub_k && tid == 0) publish_release(p.prog + u, -1);
         return;
     }
     // the layout is copied into LDS: a reference into device memory would be
@@ -1187,7 +1187,7 @@ __global__ __launch_bounds__(kT) void search_kernel(Params p)
         // for readers possibly on another chiplet)
         if (p.pub_k && (k + 1) % p.pub_k == 0 && k < Tp) {
             block_sync_vm();
-            if (tid == 0) __hip_atomic_store(p.prog + u, k + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) publish_release(p.prog + u, k + 1);
         }
     }
     if (tid == 0) {
@@ -1202,7 +1202,7 @@ __global__ __launch_bounds__(kT) void search_kernel(Params p)
     }
     if (p.pub_k) {
         block_sync_vm();
-        if (tid == 0) __hip_atomic_store(p.prog + u, rc == 0 ? Tp + 1 : -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) publish_release(p.prog + u, rc == 0 ? Tp + 1 : -1);
     }
 }
 
