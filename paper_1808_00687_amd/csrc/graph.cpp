@@ -36,6 +36,10 @@ extern "C" const char *wfst_last_error(void) { return wfd::last_error(); }
 
 namespace {
 
+// 16-byte units of the node array: per cache line, and the id limit.
+constexpr int kLineUnits = 8;
+constexpr int64_t kMaxUnits = 0x7FFFFFFFLL;
+
 int fail(int code, const char *msg)
 {
     set_error("%s", msg);
@@ -213,11 +217,20 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
         // compaction a survivor's rows shares a cache line with the first
         // arcs the next expansion reads.  Ids keep the states' order (ties
         // broken by the lowest id stay the same).
+        // A state whose records and arcs fit one cache line does not straddle
+        // two: every random access to a state then fetches one line
+        // (unless the padding would push the ids past 31 bits).
         hdr_pos.resize(static_cast<size_t>(n));
-        for (int32_t s = 0; s < n; s++) {
-            hdr_pos[s] = static_cast<int32_t>(n_units);
-            n_units += 2 + (eoff[s + 1] - eoff[s]);
-            if (n_units >= 0x7FFFFFFFLL) return fail(WFST_EINVAL, "wfst_load: graph too large (2^31 16-byte units)");
+        for (int line = kLineUnits;; line = 1) {
+            n_units = 0;
+            for (int32_t s = 0; s < n && n_units < kMaxUnits; s++) {
+                const int64_t units = 2 + (eoff[s + 1] - eoff[s]);
+                if (units <= line && n_units % line + units > line) n_units += line - n_units % line;
+                hdr_pos[s] = static_cast<int32_t>(n_units);
+                n_units += units;
+            }
+            if (n_units < kMaxUnits) break;
+            if (line == 1) return fail(WFST_EINVAL, "wfst_load: graph too large (2^31 16-byte units)");
         }
         auto remap = [&](int32_t x) {   // keeps the has-epsilon flag
             return hdr_pos[x & 0x7FFFFFFF] | (x & static_cast<int32_t>(0x80000000u));
