@@ -118,6 +118,8 @@ inline int32_t user_state(const Graph &g, int32_t dev)
     return static_cast<int32_t>(it - g.hdr_pos.begin()) - 1;
 }
 
+constexpr int kSetMid = 1, kSetLarge = 2;   // UttState::big_sets
+
 // Per-utterance decode state in device memory.
 struct UttState {
     const float *ll;      // [T x L] log-likelihoods (device)
@@ -127,7 +129,7 @@ struct UttState {
     int32_t gframes;      // frames whose token table overflowed LDS (redone in device memory)
     // written by the search kernel when it ends
     int32_t n_last;       // |S_T'|
-    int32_t big_sets;     // some token set is too large for the record kernel's LDS table
+    int32_t big_sets;     // kSetMid, kSetLarge: some token set is too large for the record kernel's small table, for any
     int64_t n_tok;        // survivors of all token sets
     int64_t le_cnt;       // emitting lattice records
     int64_t lx_cnt;       // epsilon lattice records

@@ -25,26 +25,48 @@
 //      above its destination).  The start token of S_0 has no such arc.
 // The search reserved each set's regions (one entry per emitting and per
 // epsilon out-arc of the set); the block appends into them and stores the
-// counts.  Sets larger than the LDS table are left to a second launch with a
-// larger LDS table (or, beyond that, the utterance's device-memory table).
+// counts.  Sets larger than the LDS table are left to a second launch, and
+// those beyond that one's to a third with a larger LDS table still (or the
+// utterance's device-memory table).
 #include "record_set.h"
 
 namespace wfd {
 
 namespace {
 
-// One block per (set k, utterance u) whose set fits the LDS table.
-__global__ __launch_bounds__(kRT) void record_kernel(Params p)
+constexpr int kXcds = 8;   // chiplets, which take the blocks of a launch in turn
+// Up to this many sets one launch with the middle table takes all: they are
+// few blocks per CU, and a second launch costs more than two blocks on a CU
+// gain (one utterance of 336 decoded frames through fixed buffers: 0.899 ms
+// with one launch, 0.908 with two; 64 utterances of 300-1500 frames: 31.3 and
+// 30.7).
+constexpr int kOneLaunch = 2048;
+
+// One block per (set k, utterance u), for the sets that fit its table and not
+// the smaller one's.  Blocks are given to the eight chiplets in turn: block x
+// takes its set from the x % 8-th eighth of the utterance's frames, so that
+// the states that consecutive sets share meet in one L2 (256 utterances of
+// 300-1500 frames: 49.3 ms, against 49.8 with frame x in block x).
+template <typename L, int kBelow>
+__global__ __launch_bounds__(kRT, L::kTabBits == RecSmall::kTabBits ? 8 : 4) void record_kernel(Params p)
 {
-    __shared__ uint32_t s_keys[kRSlots];
-    __shared__ int32_t s_vals[kRSlots];
-    __shared__ unsigned long long s_win[kRFill];
+    __shared__ L l;
     __shared__ RSh sh;
-    const int k = blockIdx.x;
     const int u = blockIdx.y;
-    const UttState &st = p.st[u];
-    if (st.status != 0 || k > st.Tp) return;
-    record_one(p, u, k, s_keys, s_vals, s_win, sh);
+    UttState &st = p.st[u];
+    const int per = (st.Tp + kXcds) / kXcds;   // ceil((Tp + 1) / kXcds)
+    const int at = blockIdx.x / kXcds;
+    const int k = (blockIdx.x % kXcds) * per + at;
+    if (st.status != 0 || at >= per || k > st.Tp || (kBelow > 0 && !(st.big_sets & kSetMid))) return;
+    const int n = set_size(p, p.lay[u], k);
+    if (n <= kBelow) return;
+    const int cap = min(kRFill, p.rec_fill);
+    if (n > min(L::kFill, cap)) {
+        // left to the next launch, or to the large-set pass
+        if (threadIdx.x == 0) atomicOr(&st.big_sets, n > cap ? kSetLarge : kSetMid);
+        return;
+    }
+    record_one(p, u, k, n, l, sh);
 }
 
 // The sets too large for record_kernel's table: kLargeParts blocks per
@@ -60,14 +82,15 @@ constexpr int kRBigFill = (1 << kRBigBits) / 4 * 3;
 __global__ __launch_bounds__(kRT) void record_large_kernel(Params p)
 {
     __shared__ uint32_t s_keys[1 << kRBigBits];
-    __shared__ int32_t s_vals[1 << kRBigBits];
+    __shared__ uint32_t s_ckey[kRBigFill];
+    __shared__ uint16_t s_vals[1 << kRBigBits];
     __shared__ RSh sh;
     __shared__ int s_list[kRT];
     __shared__ int s_n;
     const int u = blockIdx.x;
     const int part = blockIdx.y;
     const UttState &st = p.st[u];
-    if (st.status != 0 || !st.big_sets) return;
+    if (st.status != 0 || !(st.big_sets & kSetLarge)) return;
     const UttLayout &ly = p.lay[u];
     RTab<true> gt;
     const int64_t gbase = static_cast<int64_t>(u) * p.capG;
@@ -97,17 +120,19 @@ __global__ __launch_bounds__(kRT) void record_large_kernel(Params p)
                 RTab<false> t;
                 t.keys = s_keys;
                 t.vals = s_vals;
+                t.ckey = s_ckey;
                 t.mask = (1u << bits) - 1u;
                 t.shift = 32 - bits;
                 t.mul = p.hash_mul;
                 for (int j = threadIdx.x; j < (1 << bits); j += blockDim.x) s_keys[j] = kEmptyKey;
                 __syncthreads();
-                record_set<false, true>(p, u, kk, t, win, sh, lin_e(p, ly, kk), lin_x(p, ly, kk));
+                record_set<false, true, 0>(p, u, kk, t, win, sh, lin_e(p, ly, kk), lin_x(p, ly, kk), nullptr);
             } else {
                 if (part != 0) continue;
                 for (int64_t j = threadIdx.x; j < p.capG; j += blockDim.x) gt.keys[j] = kEmptyKey;
+                gt.ckey = p.sv_key + ly.sv0 + p.sv_off[ly.fo0 + kk];
                 __syncthreads();
-                record_set<true, true>(p, u, kk, gt, win, sh, lin_e(p, ly, kk), lin_x(p, ly, kk));
+                record_set<true, true, 0>(p, u, kk, gt, win, sh, lin_e(p, ly, kk), lin_x(p, ly, kk), nullptr);
             }
             __syncthreads();
         }
@@ -288,9 +313,7 @@ __device__ int prune_chunk(const Params &p, int u, const UttLayout &ly, int a, i
 
 __global__ __launch_bounds__(kRT) void lattice_stream_kernel(Params p)
 {
-    __shared__ uint32_t s_keys[kRSlots];
-    __shared__ int32_t s_vals[kRSlots];
-    __shared__ unsigned long long s_win[kRFill];
+    __shared__ RecMid l;
     __shared__ LSh sh;
     const int u = blockIdx.x;
     UttState &st = p.st[u];
@@ -340,21 +363,14 @@ __global__ __launch_bounds__(kRT) void lattice_stream_kernel(Params p)
             const int n = static_cast<int>(so[k + 1] - so[k]);
             const RecOut eo{re, k > 0 ? rle[k - 1] : 0, p.rce}, xo{rx, rlx[k], p.rcx};
             if (n <= min(kRFill, p.rec_fill)) {
-                int bits = 10;
-                while (bits < kRSlotBits && (1 << bits) < 2 * n) bits++;
-                RTab<false> t;
-                t.keys = s_keys;
-                t.vals = s_vals;
-                t.mask = (1u << bits) - 1u;
-                t.shift = 32 - bits;
-                t.mul = p.hash_mul;
-                for (int i = threadIdx.x; i < (1 << bits); i += blockDim.x) s_keys[i] = kEmptyKey;
+                const RTab<false> t = rec_table(p, l, n);
                 __syncthreads();
-                record_set<false, false>(p, u, k, t, s_win, sh.r, eo, xo);
+                record_set<false, false, RecMid::kRow>(p, u, k, t, l.win, sh.r, eo, xo, l.row);
             } else {
                 for (int64_t j = threadIdx.x; j < p.capG; j += blockDim.x) gt.keys[j] = kEmptyKey;
+                gt.ckey = p.sv_key + ly.sv0 + so[k];
                 block_sync_vm();
-                record_set<true, true>(p, u, k, gt, p.sv_win + ly.sv0 + so[k], sh.r, eo, xo);
+                record_set<true, true, 0>(p, u, k, gt, p.sv_win + ly.sv0 + so[k], sh.r, eo, xo, nullptr);
             }
             rec = k + 1;
             __syncthreads();
@@ -387,8 +403,17 @@ hipError_t launch_record_large(const Params &p, hipStream_t s)
 
 hipError_t launch_record(const Params &p, int max_frames, hipStream_t s)
 {
-    hipLaunchKernelGGL(record_kernel, dim3(max_frames + 1, p.U), dim3(kRT), 0, s, p);
-    hipError_t e = hipGetLastError();
+    const dim3 grid((max_frames + kXcds) / kXcds * kXcds, p.U);
+    hipError_t e;
+    if (static_cast<int64_t>(max_frames + 1) * p.U <= kOneLaunch) {
+        hipLaunchKernelGGL((record_kernel<RecMid, 0>), grid, dim3(kRT), 0, s, p);
+    } else {
+        hipLaunchKernelGGL((record_kernel<RecSmall, 0>), grid, dim3(kRT), 0, s, p);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((record_kernel<RecMid, RecSmall::kFill>), grid, dim3(kRT), 0, s, p);
+    }
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_record_large(p, s);
 }

@@ -974,9 +974,7 @@ struct RecLds {
     int item;
     int prog;
     int seen[kRecMaxUtts];
-    unsigned long long win[kRFill];
-    uint32_t keys[kRSlots];
-    int32_t vals[kRSlots];
+    RecMid l;
 };
 
 __device__ __forceinline__ void record_role(const Params &p, RecLds &r)
@@ -1034,7 +1032,9 @@ __device__ __forceinline__ void record_role(const Params &p, RecLds &r)
             __syncthreads();
             if (r.seen[u] <= k) continue;
         }
-        record_one(p, u, k, r.keys, r.vals, r.win, r.rsh);
+        const int n = set_size(p, p.lay[u], k);
+        if (n <= min(kRFill, p.rec_fill)) record_one(p, u, k, n, r.l, r.rsh);
+        else if (tid == 0) atomicOr(&st.big_sets, kSetLarge);   // left to the large-set pass
         __syncthreads();
     }
 }
