@@ -1049,7 +1049,7 @@ int run_batch(const Graph &G, int U, const float *const *ll_in, const int32_t *T
         }
         tm.start(q);
         chk(launch_final(pg, q));
-        chk(launch_finish(pg, q));
+        chk(launch_finish(pg, Tg, q));
         tm.stop(PH_FINAL, q);
         if (g > 0) {
             hipEvent_t join = event_pool().get(G.device);
@@ -1786,7 +1786,7 @@ int noalloc_impl(const wfst_graph *gh, const float *ll, int32_t T, int32_t L, co
     chk(launch_search(p, s));
     chk(launch_record(p, T, s));
     chk(launch_final(p, s));
-    chk(launch_finish(p, s));
+    chk(launch_finish(p, T, s));
     chk(hipMemcpyAsync(&st, p.st, sizeof(UttState), hipMemcpyDeviceToHost, s));
     chk(hipStreamSynchronize(s));
     if (e != hipSuccess) return hip_fail(e, "wfst_decode_noalloc: search");

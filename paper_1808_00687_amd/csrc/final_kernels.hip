@@ -1177,6 +1177,176 @@ __device__ void lattice_block(const Params &p, int u, uint32_t *s_e, float *s_c,
     }
 }
 
+// ---------------------------------------------------------------------------
+// Chunk pruning before the backward pass.  The pass is a serial chain over the
+// token sets whose steps cost more the more records a set has, and of a large
+// set's raw records only a few percent are kept.  Here every chunk of
+// kTrimSets source sets of an utterance is pruned by a block of its own, side
+// by side: with the extra cost of every token of the set behind the chunk
+// taken as 0, the backward pass through the chunk gives each record a lower
+// bound of its extra cost (final extra costs are >= 0 and each step
+// fl(fl(p - c) + e) is monotone in e).  A record whose bound exceeds the
+// lattice beam is kept by no pass, and a node with an extra cost within the
+// beam keeps the record that gives it, so the backward pass over what is left
+// finds the same kept arcs and extra costs bit for bit.  What is left stays
+// at the front of the set's region (a round's records are read before any is
+// written, and are written no further back than they were read).
+// A set beyond the LDS arrays is left whole and counts as 0 for the set before
+// it, as the set behind the chunk does; the last set's epsilon records are
+// left whole too.
+//
+// Which utterances: a block's own chain is 2-3 us a set, so shorter ones wait
+// longer for the chunks than their backward pass gains (one of 82 frames:
+// 0.71 ms without, 0.77 with; one of 336: 0.916 and 0.952), and small raw sets
+// cost the backward pass little.  Shorter chunks leave more records (64
+// utterances: 29.9 ms with 16 sets, 29.35 with 32).  Tables of 4096 survivors
+// and half the waves let four blocks share a CU, which counts where the blocks
+// are many (256 utterances: 48.7 ms, 49.5 with 8192); a launch of few blocks
+// takes 8192, which the larger sets need.
+// Measured, lattice pass with the trimming: one utterance of 1000 frames and
+// about 1150 raw records a set 2.26 -> 1.33 ms, 64 of 300-1500 frames (the
+// longest) 3.5 -> 1.9.
+// ---------------------------------------------------------------------------
+constexpr int kTrimSets = 32;      // source sets of a chunk
+constexpr int kTrimFrames = 512;   // decoded frames from which an utterance is trimmed
+constexpr int kTrimBlocks = 512;   // blocks up to which the larger table is used
+constexpr int kTrimR = 2;          // records per thread and round
+constexpr int kTrimAvg = 64;       // raw records per set up to which an utterance is left as it is
+
+// The kept ones (kp) of a round's records to the front of the region, by the
+// whole wave; *cnt counts those of the region so far.
+__device__ __forceinline__ void trim_append(int4 *out, int *cnt, bool kp, const int4 &x)
+{
+    const uint64_t m = __ballot(kp);
+    if (!m) return;
+    int b = 0;
+    if (lane_id() == 0) b = atomicAdd(cnt, __popcll(m));
+    b = __builtin_amdgcn_readlane(b, 0);
+    if (kp) out[b + rank_in(m)] = x;
+}
+
+template <int kTrimT, int kTrimCap>
+__global__ __launch_bounds__(kTrimT, 8) void lattice_trim_kernel(Params p)
+{
+    __shared__ uint32_t s_e[2][kTrimCap];   // extra-cost keys of S_j+1 and S_j
+    __shared__ int cnt[2], flag[3];
+    const int tid = threadIdx.x;
+    const int u = blockIdx.y;
+    const UttState &st = p.st[u];
+    const int Tp = st.Tp;
+    const int a = blockIdx.x * kTrimSets;
+    if (st.status != 0 || a >= Tp || Tp < kTrimFrames || st.le_cnt + st.lx_cnt <= static_cast<int64_t>(kTrimAvg) * (Tp + 1)) return;
+    const UttLayout ly = p.lay[u];
+    const int b = min(a + kTrimSets, Tp);
+    const float lb = p.lattice_beam;
+    const uint32_t kinf = okey(__int_as_float(0x7F800000));
+    const uint32_t *tok = p.sv_key + ly.sv0;
+    const int64_t *so = p.sv_off + ly.fo0;
+    const int cap = min(kTrimCap, p.lat_lds);
+    bool zero = true;   // the tokens of S_j+1 count as 0
+    int h = 0;          // the half of S_j+1
+    for (int j = b - 1; j >= a; j--, h ^= 1) {
+        const int64_t b0 = so[j], a0 = so[j + 1];
+        const int nB = static_cast<int>(a0 - b0);
+        if (nB > cap) {
+            zero = true;
+            continue;
+        }
+        const int ne = static_cast<int>(p.le_cnt[ly.fo0 + j]), nx = static_cast<int>(p.lx_cnt[ly.fo0 + j]);
+        int4 *re = p.lat_e + ly.le0 + p.le_off[ly.fo0 + j];
+        int4 *rx = p.lat_x + ly.lx0 + p.lx_off[ly.fo0 + j];
+        const uint32_t *eA = s_e[h];
+        uint32_t *eB = s_e[h ^ 1];
+        // (the last set's reads of what is cleared here are behind its last barrier)
+        for (int i = tid; i < nB; i += kTrimT) eB[i] = kinf;
+        if (tid < 2) cnt[tid] = 0;
+        if (tid < 3) flag[tid] = 0;
+        __syncthreads();
+        // emitting records
+        for (int r0 = 0; r0 < ne; r0 += kTrimT * kTrimR) {
+            int4 x[kTrimR];
+            uint32_t c[kTrimR];
+            bool kp[kTrimR];
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) {
+                const int i = r0 + q * kTrimT + tid;
+                x[q] = re[min(i, ne - 1)];
+            }
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) c[q] = tok[x[q].y];
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) {
+                const float e = zero ? 0.0f : okey_val(eA[x[q].y - a0]);
+                const float d1 = __int_as_float(x[q].w) - okey_val(c[q]);
+                const float ex = d1 + e;
+                const bool in = r0 + q * kTrimT + tid < ne;
+                kp[q] = in && !(ex > lb);
+                if (in) atomicMin(eB + (x[q].x - b0), okey(ex));
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) trim_append(re, &cnt[0], kp[q], x[q]);
+        }
+        // epsilon records, to their fixed point
+        if (nx > 0) {
+            __syncthreads();
+            int4 x[kTrimR];
+            float cc[kTrimR];
+            bool kp[kTrimR];
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) x[q] = rx[min(q * kTrimT + tid, nx - 1)];
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) cc[q] = okey_val(tok[x[q].y]);
+            for (int it = 0;; it++) {
+                if (tid == 0) flag[(it + 1) % 3] = 0;
+                bool changed = false;
+#pragma unroll
+                for (int q = 0; q < kTrimR; q++) {
+                    const float d1 = __int_as_float(x[q].w) - cc[q];
+                    const float ex = d1 + okey_val(eB[x[q].y - b0]);
+                    const uint32_t k = okey(ex);
+                    const bool in = q * kTrimT + tid < nx;
+                    kp[q] = in && !(ex > lb);
+                    if (in && k < eB[x[q].x - b0]) {
+                        atomicMin(eB + (x[q].x - b0), k);
+                        changed = true;
+                    }
+                }
+                for (int i = kTrimR * kTrimT + tid; i < nx; i += kTrimT) {
+                    const int4 y = rx[i];
+                    const float d1 = __int_as_float(y.w) - okey_val(tok[y.y]);
+                    const uint32_t k = okey(d1 + okey_val(eB[y.y - b0]));
+                    if (k < eB[y.x - b0]) {
+                        atomicMin(eB + (y.x - b0), k);
+                        changed = true;
+                    }
+                }
+                if (changed) flag[it % 3] = 1;
+                __syncthreads();
+                if (!flag[it % 3]) break;
+            }
+            // (the last round changed nothing: its bounds are final)
+#pragma unroll
+            for (int q = 0; q < kTrimR; q++) trim_append(rx, &cnt[1], kp[q], x[q]);
+            for (int r0 = kTrimR * kTrimT; r0 < nx; r0 += kTrimT) {
+                const int i = r0 + tid;
+                const int4 y = rx[min(i, nx - 1)];
+                const float d1 = __int_as_float(y.w) - okey_val(tok[y.y]);
+                const float ex = d1 + okey_val(eB[y.y - b0]);
+                __syncthreads();
+                trim_append(rx, &cnt[1], i < nx && !(ex > lb), y);
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            p.le_cnt[ly.fo0 + j] = cnt[0];
+            p.lx_cnt[ly.fo0 + j] = cnt[1];
+        }
+        __syncthreads();
+        zero = false;
+    }
+}
+
 // Blocks [0, U): backtrace of utterance b; blocks [U, 2U) (with a lattice):
 // lattice-beam pruning of utterance b - U.  The two are independent and run
 // side by side.
@@ -1469,8 +1639,19 @@ hipError_t launch_pack_paths(const Params &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_finish(const Params &p, hipStream_t s)
+hipError_t launch_finish(const Params &p, int max_frames, hipStream_t s)
 {
+    // (what the incremental pass leaves is pruned already, and an infinite
+    // beam keeps everything)
+    if (p.lattice && !p.stream_k && p.lattice_beam < __builtin_huge_valf() && max_frames >= kTrimFrames) {
+        const dim3 grid((max_frames + kTrimSets - 1) / kTrimSets, p.U);
+        if (static_cast<int64_t>(grid.x) * p.U <= kTrimBlocks)
+            hipLaunchKernelGGL((lattice_trim_kernel<1024, 8192>), grid, dim3(1024), 0, s, p);
+        else
+            hipLaunchKernelGGL((lattice_trim_kernel<512, 4096>), grid, dim3(512), 0, s, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(finish_kernel, dim3(p.lattice ? 2 * p.U : p.U), dim3(kLatT), 0, s, p);
     return hipGetLastError();
 }

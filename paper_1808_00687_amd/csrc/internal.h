@@ -301,7 +301,7 @@ hipError_t launch_record(const Params &p, int max_frames, hipStream_t s);
 // launch with record workgroups)
 hipError_t launch_record_large(const Params &p, hipStream_t s);
 hipError_t launch_lattice_stream(const Params &p, hipStream_t s);
-hipError_t launch_finish(const Params &p, hipStream_t s);
+hipError_t launch_finish(const Params &p, int max_frames, hipStream_t s);
 hipError_t launch_pack_paths(const Params &p, hipStream_t s);
 hipError_t launch_lattice_emit(const Params &p, int max_frames, hipStream_t s);
 hipError_t launch_zero(void *ptr, size_t bytes, hipStream_t s);   // ptr 16-byte aligned, bytes % 4 == 0
