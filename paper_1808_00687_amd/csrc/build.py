@@ -34,6 +34,8 @@ FLAGS = [
     "-fno-fast-math",
     "-fno-gpu-flush-denormals-to-zero",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # atomics by one lane of a wave stay one instruction
+    "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
     "-Wall",
     "-I", INCLUDE,
     "-I", HERE,

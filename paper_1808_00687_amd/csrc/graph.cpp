@@ -39,6 +39,9 @@ namespace {
 // 16-byte units of the node array: per cache line, and the id limit.
 constexpr int kLineUnits = 8;
 constexpr int64_t kMaxUnits = 0x7FFFFFFFLL;
+// -0.0f: a weight a closure path does not have (x + -0 = x for every x)
+constexpr int32_t kNoWeight = static_cast<int32_t>(0x80000000u);
+constexpr int32_t kInfWeight = 0x7F800000;   // +inf
 
 int fail(int code, const char *msg)
 {
@@ -160,8 +163,8 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
         }
         // Epsilon-closure lists: for a state whose epsilon paths number at
         // most kClosureMax and are at most kClosureDepth arcs long, every
-        // such path as one entry {last destination, last arc, length, the
-        // path's weights in order}.  Children come before parents in reverse
+        // such path as one entry {last destination, the path's weights in
+        // order}.  Children come before parents in reverse
         // topological order, so a state's list is its arcs followed by each
         // child's list behind the arc to it.
         std::vector<int32_t> cl_size(static_cast<size_t>(n), 0), cl_depth(static_cast<size_t>(n), 0);
@@ -186,18 +189,20 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
             for (int32_t x = xoff[s]; x < xoff[s + 1]; x++) {
                 const int4 r = xarc[x];
                 const int32_t d = r.x & 0x7FFFFFFF;
-                ctab.push_back(make_int4(d, r.z, 1, r.y));
-                ctab.push_back(make_int4(0, 0, 0, 0));
-                ctab.push_back(make_int4(0, 0, 0, 0));
+                ctab.push_back(make_int4(d, r.y, kNoWeight, kNoWeight));
+                ctab.push_back(make_int4(kNoWeight, kNoWeight, kNoWeight, kNoWeight));
+                ctab.push_back(make_int4(kNoWeight, kNoWeight, 1, 0));
                 if (cl_size[d] == 0) continue;
                 for (int32_t i = 0; i < cl_size[d]; i++) {
                     const size_t ci = kClosureStride * static_cast<size_t>(cl_off[d] + i);
                     const int4 c0 = ctab[ci], c1 = ctab[ci + 1], c2 = ctab[ci + 2];
                     // the arc to d, then the child's path (at most
                     // kClosureDepth - 1 arcs, so its last weight slot is free)
-                    ctab.push_back(make_int4(c0.x, c0.y, c0.z + 1, r.y));
+                    const int32_t len = c2.z + 1;
+                    const uint32_t longer = len > kClosureShort ? 0x80000000u : 0u;
+                    ctab.push_back(make_int4((c0.x & 0x7FFFFFFF) | static_cast<int32_t>(longer), r.y, c0.y, c0.z));
                     ctab.push_back(make_int4(c0.w, c1.x, c1.y, c1.z));
-                    ctab.push_back(make_int4(c1.w, c2.x, c2.y, c2.z));
+                    ctab.push_back(make_int4(c1.w, c2.x, len, 0));
                 }
             }
             cl_off[s] = off;
@@ -224,7 +229,7 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
         for (int line = kLineUnits;; line = 1) {
             n_units = 0;
             for (int32_t s = 0; s < n && n_units < kMaxUnits; s++) {
-                const int64_t units = 2 + (eoff[s + 1] - eoff[s]);
+                const int64_t units = 2 + std::max(1, eoff[s + 1] - eoff[s]);
                 if (units <= line && n_units % line + units > line) n_units += line - n_units % line;
                 hdr_pos[s] = static_cast<int32_t>(n_units);
                 n_units += units;
@@ -232,7 +237,7 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
             if (n_units < kMaxUnits) break;
             if (line == 1) return fail(WFST_EINVAL, "wfst_load: graph too large (2^31 16-byte units)");
         }
-        auto remap = [&](int32_t x) {   // keeps the has-epsilon flag
+        auto remap = [&](int32_t x) {   // keeps the top bit
             return hdr_pos[x & 0x7FFFFFFF] | (x & static_cast<int32_t>(0x80000000u));
         };
         node.assign(static_cast<size_t>(n_units), make_int4(0, 0, 0, 0));
@@ -241,7 +246,8 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
         for (int32_t s = 0; s < n; s++) {
             const int64_t h = hdr_pos[s];
             const int32_t deg = eoff[s + 1] - eoff[s];
-            node[h] = make_int4(static_cast<int32_t>(h + 2), static_cast<int32_t>(h + 2 + deg), xoff[s], xoff[s + 1]);
+            node[h] = make_int4(deg, static_cast<int32_t>(h + 2 + std::max(deg, 1)), xoff[s], xoff[s + 1]);
+            if (deg == 0) node[h + 2] = make_int4(static_cast<int32_t>(h), 0, kInfWeight, 0);
             int4 x0 = srec[2 * static_cast<size_t>(s) + 1];
             if (xoff[s + 1] > xoff[s]) x0.x = remap(x0.x);
             node[h + 1] = x0;
@@ -254,7 +260,7 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
             if (final_weight) node_fin[h] = final_weight[s];
         }
         for (auto &r : xarc) r.x = remap(r.x);
-        for (size_t i = 0; i < ctab.size(); i += kClosureStride) ctab[i].x = hdr_pos[ctab[i].x];
+        for (size_t i = 0; i < ctab.size(); i += kClosureStride) ctab[i].x = remap(ctab[i].x);
         for (int64_t a = 0; a < e; a++)
             if (ilabel[a]) uarc[a].y = hdr_pos[src[a]] + 2 + (uarc[a].y - eoff[src[a]]);
         std::vector<int4>().swap(earc);

@@ -60,14 +60,18 @@ constexpr uint32_t kHashMulAlt = 0x85EBCA77u;
 // The graph on the device.  States are numbered by the position of their
 // first record in `node`, an array of 16-byte units where each state's two
 // records are followed by its emitting arcs:
-//   node[s]     = {first emitting arc, end of its emitting arcs (both unit
-//                  indices into node), first and end epsilon record in xarc}
+//   node[s]     = {number of its emitting arcs, end of their records (a unit
+//                  index into node; they begin at s + 2), first and end
+//                  epsilon record in xarc}
 //   node[s + 1] = the state's first epsilon record (destination, weight,
 //                  user arc) with the state's closure word as its 4th word
 //                  ((first entry + 1) << kClosureSizeBits | size - 1, 0 if
 //                  it has no list)
 //   node[a]     = an emitting arc: {dst | has-epsilon bit << 31, ilabel - 1,
-//                  weight bits, closure word of dst}
+//                  weight bits, closure word of dst}; a state without any
+//                  holds one record of weight +inf (into itself, column 0),
+//                  whose candidates never survive: every token then has an
+//                  arc record, which is what finding an arc's token relies on
 // Ids keep the order of the user's state ids; Graph::hdr_pos maps back.
 struct DevGraph {
     int32_t n;
@@ -81,7 +85,8 @@ struct DevGraph {
     const int4 *xarc;   // epsilon records by source: {dst | has-epsilon bit, weight, user arc, closure word of dst}
     const int32_t *arc_src;
     const float *final_w;   // by device id (0 elsewhere), or NULL
-    const int4 *ctab;   // closure entries, 3 x int4 each: {dst, user arc, path length, w0}, {w1..w4}, {w5..w8}
+    const int4 *ctab;   // closure entries, 3 x int4 each: {dst | longer than kClosureShort << 31, w0..w2}, {w3..w6},
+                        // {w7, w8, path length, 0}; weights the path does not have are -0
     const int2 *uarc;   // per user arc: {olabel, index of its record in node or xarc}
 };
 
@@ -92,6 +97,7 @@ struct DevGraph {
 constexpr int kClosureSizeBits = 8;
 constexpr int kClosureMax = 1 << kClosureSizeBits;
 constexpr int kClosureDepth = 9;
+constexpr int kClosureShort = 7;    // arcs of a path whose weights fit the first two words
 constexpr int kClosureStride = 3;   // int4 words per entry
 constexpr int64_t kClosureEntries = (int64_t{1} << (32 - kClosureSizeBits)) - 2;
 
@@ -135,6 +141,7 @@ struct UttState {
     int64_t lx_cnt;       // epsilon lattice records
     int64_t arcs_expanded;
     int64_t eps_arcs;
+    int64_t le_slots;     // emitting lattice-record slots reserved
     // final
     int32_t final_sv;
     int32_t final_state;
@@ -203,7 +210,6 @@ struct Params {
     uint32_t *sv_key;         // ordered key of the token cost
     int32_t *sv_prev;         // survivor the back-pointer arc leaves from (-1 for the start token)
     int32_t *sv_arc;          // back-pointer user arc (-1 for the start token)
-    int32_t *sv_ebeg;         // first emitting arc record of the survivor's state
     int32_t *sv_epre;         // exclusive prefix of emitting out-degree within the token set
     unsigned long long *sv_win;   // record pass scratch for sets beyond its LDS table:
                                   // (user arc + 1) << 32 | source survivor of the winning arc
@@ -249,6 +255,7 @@ struct Params {
     int32_t *rec_next;
     int32_t lat_pipe;         // the lattice backward pass's streamed form: -1 never, 0 where sets are
                               // small on average, 1 wherever it fits
+    int32_t ahead;            // the search fetches the lines of claimed states ahead of their use
     int32_t lat_spin;         // > 0: polls of one flag before a lattice pass's wait gives up (else its own)
 };
 

@@ -236,7 +236,7 @@ __device__ void record_set(const Params &p, int u, int k, const RTab<G> &t, unsi
                 const int pre_i = p.sv_epre[ly.sv0 + b1 + i];
                 const int nxt = i + 1 < n1 ? p.sv_epre[ly.sv0 + b1 + i + 1] : a1;
                 deg = nxt - pre_i;
-                eb = p.sv_ebeg[ly.sv0 + b1 + i];
+                eb = sv_state[b1 + i] + 2;   // a state's arcs follow its two records
                 cst = okey_val(sv_key[b1 + i]);
             }
             const int incl = wave_incl_scan(deg);

@@ -1,0 +1,50 @@
+"""The search's three token tables at their limits, exact against the oracle.
+
+A start state with a loop (column 0), an arc into each of n states (column 1),
+which have an arc to the next of them (column 2) and one back (column 3), but
+every third only an epsilon arc to the next state: a dead end without emitting
+arcs until its closure.  A frame lets only one column's arcs into the beam, so
+that a token set holds one, two or n survivors.  n lies on both sides of what
+the small table's copy of a set holds (2496), of the states the small table
+takes (6144) and of those the big one takes (12800); the frames walk from one
+table to the next and back.  The rows' widths are no multiple of a fetch.
+"""
+import numpy as np
+import pytest
+
+from paper_1808_00687_amd import workloads as W
+import parity
+from test_gpu_parity import dec, to_dev, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("max_active", [0, 2000])
+@pytest.mark.parametrize("n,cols", [(2495, 4), (2496, 67), (2497, 1025), (6143, 7), (6144, 4099), (6145, 9),
+                                    (12799, 5), (12800, 6), (12801, 1023)])
+def test_search_table_edges(dec, torch_mod, oracle_mod, n, cols, max_active):  # noqa: F811
+    rng = np.random.default_rng(n)
+    ids = np.arange(1, n + 1)
+    dead = ids[(ids % 3 == 0) & (ids < n)]
+    live = np.setdiff1d(ids, dead)
+    zero = np.zeros(n, np.int64)
+    src = np.concatenate([[0], zero, live, live, dead])
+    dst = np.concatenate([[0], ids, live % n + 1, live * 0, dead + 1])
+    col = np.concatenate([[0], zero + 1, live * 0 + 2, live * 0 + 3, dead * 0 + 4])
+    order = np.argsort(src, kind="stable")
+    src, dst, col = src[order].astype(np.int32), dst[order].astype(np.int32), col[order]
+    # the columns of the four kinds of emitting arc; label 0 is epsilon
+    at = np.array([0, 1, cols - 2, cols - 1])
+    il = np.where(col < 4, np.append(at + 1, 0)[col], 0)
+    # whole-number weights: ties, decided by the lowest arc
+    g = W.Graph(n + 1, src, dst, il.astype(np.int32), np.zeros(src.size, np.int32),
+                rng.integers(0, 4, size=src.size).astype(np.float32))
+    kind = np.array([0, 1, 2, 2, 3, 0, 1, 3, 0, 1])
+    ll = np.full((kind.size, cols), -1000.0, np.float32)
+    ll[np.arange(kind.size), at[kind]] = rng.integers(-3, 4, size=kind.size)
+    ro = oracle_mod.decode(g, ll, 50.0, max_active, 4.0)
+    gh = dec.load_graph(g)
+    rg = dec.wfst_decode(gh, to_dev(torch_mod, ll), beam=50.0, max_active=max_active, lattice_beam=4.0,
+                         record_tokens=True, capacity_hint=n + 8)
+    parity.assert_same(ro, rg, lattice=True, tag="%d states, %d columns, max_active %d" % (n, cols, max_active))
+    gh.free()
