@@ -162,7 +162,6 @@ struct wfst_result {
     std::vector<int64_t> tok_off;
     std::vector<int32_t> tok_state, tok_arc;
     std::vector<float> tok_cost;
-    int64_t le_slots = 0;   // emitting lattice-record slots the search reserved
     wfst_stats stats{};
 };
 
@@ -667,6 +666,7 @@ void carve_ws(Arena &a, Params &p, int U, const Totals &tot, UttLayout **d_lay, 
     *fo_all = a.get<int64_t>(kOffsetArrays * tot.fo);
     p.blank_ids = a.get<int32_t>(p.n_blank);
     p.cut_arr = a.get<uint32_t>(tot.fo);
+    p.set_arcs = a.get<int32_t>(tot.fo);
     p.kept = a.get<int32_t>(tot.kp);
     p.path_arc = a.get<int32_t>(tot.pa);
     p.path_frame = a.get<int32_t>(tot.pa);
@@ -1167,7 +1167,6 @@ int run_batch(const Graph &G, int U, const float *const *ll_in, const int32_t *T
         r->stats.tokens_last = x.n_last;
         r->stats.arcs_expanded = x.arcs_expanded;
         r->stats.eps_arcs = x.eps_arcs;
-        r->le_slots = x.le_slots;
         r->stats.lattice_raw = x.le_cnt + x.lx_cnt;
         r->stats.lattice_kept = lattice ? x.lat_kept : 0;
         r->stats.lattice_incremental = p.stream_k ? x.lat_inc : r->stats.lattice_raw;
@@ -1301,7 +1300,7 @@ Sizes initial_sizes(const Graph &G, const wfst_decode_opts &o)
     // needed, else twice the graph's mean out-degrees
     z.em = G.rec_em.load();
     z.xm = G.rec_xm.load();
-    if (z.em <= 0) z.em = std::max<int64_t>(2, 2 * G.d.n_emit / std::max<int64_t>(N, 1) + 2);
+    if (z.em <= 0) z.em = std::max<int64_t>(2, 2 * G.d.n_emit / std::max<int64_t>(N, 1) + 1);
     if (z.xm <= 0) z.xm = std::max<int64_t>(1, 2 * G.d.n_eps / std::max<int64_t>(N, 1) + 1);
     z.capA = 0;
     return z;
@@ -1410,7 +1409,7 @@ int decode_impl(const wfst_graph *gh, int32_t n_utt, const float *const *loglike
         for (int u = 0; u < n_utt; u++) {
             const wfst_stats &x = res[u]->stats;
             const int64_t tok = std::max<int64_t>(x.tokens, 1);
-            em = std::max<int64_t>(em, (5 * res[u]->le_slots / tok) / 4 + 1);
+            em = std::max<int64_t>(em, (5 * x.arcs_expanded / tok) / 4 + 1);
             xm = std::max<int64_t>(xm, (5 * x.eps_arcs / tok) / 4 + 1);
         }
         G.rec_em.store(std::min(em, z.em));

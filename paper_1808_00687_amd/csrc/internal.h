@@ -141,7 +141,6 @@ struct UttState {
     int64_t lx_cnt;       // epsilon lattice records
     int64_t arcs_expanded;
     int64_t eps_arcs;
-    int64_t le_slots;     // emitting lattice-record slots reserved
     // final
     int32_t final_sv;
     int32_t final_state;
@@ -232,6 +231,7 @@ struct Params {
     int64_t *le_cnt;          // records in each set's regions (the record kernel writes)
     int64_t *lx_cnt;
     uint32_t *cut_arr;        // pruning cutoff key of each token set
+    int32_t *set_arcs;        // emitting arcs of each token set as sv_epre counts them (with the dead ends' placeholders)
     int32_t *kept;
     int32_t *path_arc;
     int32_t *path_frame;

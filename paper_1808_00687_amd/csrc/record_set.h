@@ -227,7 +227,7 @@ __device__ void record_set(const Params &p, int u, int k, const RTab<G> &t, unsi
     if (k > 0) {
         const int64_t b1 = so[k - 1];
         const int n1 = static_cast<int>(b0 - b1);
-        const int a1 = static_cast<int>(p.rle_off[ly.fo0 + k] - p.rle_off[ly.fo0 + k - 1]);
+        const int a1 = p.set_arcs[ly.fo0 + k - 1];
         for (int i0 = wid * kWave; i0 < n1; i0 += nw * kWave) {
             const int i = i0 + lane;
             int deg = 0, eb = 0;

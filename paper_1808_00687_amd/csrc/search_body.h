@@ -123,8 +123,7 @@ struct Sh {
 
 // Running values of the utterance, thread 0's own (in LDS: no registers held).
 struct Run {
-    int64_t le, lx;      // emitting and epsilon regions reserved so far
-    int64_t arcs;
+    int64_t le, lx;      // emitting and epsilon regions reserved so far (le: the arcs expanded, too)
     int64_t eps;         // epsilon out-arcs of the survivors
 };
 
@@ -1028,13 +1027,14 @@ __device__ __forceinline__ int frame(const Params &p, Lds &lds, const Tab<M> &t,
     if (ns == 0) return WFST_ENOPATH;
     // Token set k, its cutoff and the lattice record regions of set k: one
     // record per emitting arc of S_k (into S_k+1) at most, one per epsilon
-    // arc of S_k at most.  The emitting offsets also give the record pass
-    // the emitting arcs of each set.  (A region that would overflow is
-    // reported through sh.status: the next frame sees it after its first
-    // barrier, and the set is not published.)
+    // arc of S_k at most; a dead end's placeholder arc gives no record and
+    // reserves none, so the record pass gets the set's arcs with the
+    // placeholders apart.  (A region that would overflow is reported through
+    // sh.status: the next frame sees it after its first barrier, and the set
+    // is not published.)
     if (tid == kT - kWave) {
         Run &run = lds.run;
-        const int64_t a_rec = k < Tp ? a_kept : 0;
+        const int64_t a_rec = k < Tp ? a_kept - static_cast<int>(c.xsum >> 32) : 0;
         const int x_kept = static_cast<int>(c.xsum);
         // (with the incremental lattice pass the regions only bound the ring use
         // per set; the pass checks its own capacities)
@@ -1044,7 +1044,7 @@ __device__ __forceinline__ int frame(const Params &p, Lds &lds, const Tab<M> &t,
             run.le += a_rec;
             run.lx += x_kept;
             run.eps += x_kept;
-            run.arcs += k < Tp ? a_kept - static_cast<int>(c.xsum >> 32) : 0;
+            p.set_arcs[ly.fo0 + k] = a_kept;
             p.sv_off[ly.fo0 + k + 1] = set0 + ns;
             p.cut_arr[ly.fo0 + k] = cut;
             p.rle_off[ly.fo0 + k + 1] = run.le;
@@ -1305,9 +1305,8 @@ __global__ __launch_bounds__(kT) void search_kernel(Params p)
         if (rc == 0) rc = sh.status;
         st.n_tok = set.end;
         st.n_last = set.n;
-        st.arcs_expanded = lds.run.arcs;
+        st.arcs_expanded = lds.run.le;
         st.eps_arcs = lds.run.eps;
-        st.le_slots = lds.run.le;
         st.gframes = gframes;
         for (int i = 0; i < 7; i++) st.phase_ticks[i] = pf.ph[i];
         if (rc != 0) st.status = rc;
