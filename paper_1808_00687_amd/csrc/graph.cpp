@@ -41,7 +41,6 @@ constexpr int kLineUnits = 8;
 constexpr int64_t kMaxUnits = 0x7FFFFFFFLL;
 // -0.0f: a weight a closure path does not have (x + -0 = x for every x)
 constexpr int32_t kNoWeight = static_cast<int32_t>(0x80000000u);
-constexpr int32_t kInfWeight = 0x7F800000;   // +inf
 
 int fail(int code, const char *msg)
 {
@@ -247,7 +246,7 @@ extern "C" int wfst_load(int32_t n, int64_t e, const int32_t *src, const int32_t
             const int64_t h = hdr_pos[s];
             const int32_t deg = eoff[s + 1] - eoff[s];
             node[h] = make_int4(deg, static_cast<int32_t>(h + 2 + std::max(deg, 1)), xoff[s], xoff[s + 1]);
-            if (deg == 0) node[h + 2] = make_int4(static_cast<int32_t>(h), 0, kInfWeight, 0);
+            if (deg == 0) node[h + 2] = make_int4(static_cast<int32_t>(h), 0, kNoArc, 0);
             int4 x0 = srec[2 * static_cast<size_t>(s) + 1];
             if (xoff[s + 1] > xoff[s]) x0.x = remap(x0.x);
             node[h + 1] = x0;

@@ -69,9 +69,10 @@ constexpr uint32_t kHashMulAlt = 0x85EBCA77u;
 //                  it has no list)
 //   node[a]     = an emitting arc: {dst | has-epsilon bit << 31, ilabel - 1,
 //                  weight bits, closure word of dst}; a state without any
-//                  holds one record of weight +inf (into itself, column 0),
-//                  whose candidates never survive: every token then has an
-//                  arc record, which is what finding an arc's token relies on
+//                  holds one placeholder (into itself, column 0, weight +inf,
+//                  which no arc has) that is never offered: every token then
+//                  has an arc record, which is what finding an arc's token
+//                  relies on
 // Ids keep the order of the user's state ids; Graph::hdr_pos maps back.
 struct DevGraph {
     int32_t n;
@@ -89,6 +90,8 @@ struct DevGraph {
                         // {w7, w8, path length, 0}; weights the path does not have are -0
     const int2 *uarc;   // per user arc: {olabel, index of its record in node or xarc}
 };
+
+constexpr int32_t kNoArc = 0x7F800000;   // weight bits of a placeholder record
 
 // Epsilon-closure lists (built by wfst_load): at most kClosureMax paths of at
 // most kClosureDepth arcs per state, kClosureEntries entries in all.  The

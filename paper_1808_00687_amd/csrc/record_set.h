@@ -270,7 +270,8 @@ __device__ void record_set(const Params &p, int u, int k, const RTab<G> &t, unsi
                 for (int r = 0; r < 2; r++) {
                     const float t1 = cnd[r] + __int_as_float(y[r].z);
                     cnd[r] = t1 - lv[r];
-                    in[r] = in[r] && okey(cnd[r]) <= cut;
+                    // (a placeholder has no record slot)
+                    in[r] = in[r] && y[r].z != kNoArc && okey(cnd[r]) <= cut;
                     ua[r] = p.g.eua[in[r] ? at[r] : 0];
                 }
 #pragma unroll

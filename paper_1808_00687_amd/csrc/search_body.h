@@ -600,6 +600,9 @@ __device__ __forceinline__ void expand(const Params &p, const Tab<M> &t, Sh &sh,
         for (int r = 0; r < kChunks; r++) {
             const float t1 = cst[r] + __int_as_float(rec[r].z);
             cnd[r] = t1 - lv[r];
+            // (a placeholder is not offered: with an infinite bound it would
+            // claim a slot)
+            ok[r] = ok[r] && rec[r].z != kNoArc;
             key[r] = ok[r] ? okey(cnd[r]) : kEmptyKey;
             km = min(km, key[r]);
             d[r] = static_cast<uint32_t>(rec[r].x) & kDstMask;
