@@ -33,13 +33,14 @@ __device__ __forceinline__ uint64_t make_tok(uint32_t key, int32_t arc)
 __device__ __forceinline__ float tok_cost(uint64_t t) { return okey_val(static_cast<uint32_t>(t >> 32)); }
 __device__ __forceinline__ int32_t tok_arc(uint64_t t) { return static_cast<int32_t>(static_cast<uint32_t>(t)) - 1; }
 
+constexpr uint32_t kMaxKey = 0xFF7FFFFFu;   // okey(FLT_MAX)
+
 // Key of the largest cost a token may keep: fl(best + beam), never +inf.
 __device__ __forceinline__ uint32_t beam_limit(uint32_t best_key, float beam)
 {
-    const uint32_t kmax = 0xFF7FFFFFu;   // okey(FLT_MAX)
-    if (best_key == kEmptyKey) return kmax;
+    if (best_key == kEmptyKey) return kMaxKey;
     uint32_t k = okey(okey_val(best_key) + beam);
-    return k < kmax ? k : kmax;
+    return k < kMaxKey ? k : kMaxKey;
 }
 
 // Early-drop bound during expansion: any candidate above fl(m + beam),

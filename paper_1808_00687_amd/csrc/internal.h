@@ -70,9 +70,9 @@ constexpr uint32_t kHashMulAlt = 0x85EBCA77u;
 //   node[a]     = an emitting arc: {dst | has-epsilon bit << 31, ilabel - 1,
 //                  weight bits, closure word of dst}; a state without any
 //                  holds one placeholder (into itself, column 0, weight +inf,
-//                  which no arc has) that is never offered: every token then
-//                  has an arc record, which is what finding an arc's token
-//                  relies on
+//                  which no arc has), whose candidates cost +inf and are
+//                  above every bound: every token then has an arc record,
+//                  which is what finding an arc's token relies on
 // Ids keep the order of the user's state ids; Graph::hdr_pos maps back.
 struct DevGraph {
     int32_t n;

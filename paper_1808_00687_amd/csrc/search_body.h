@@ -600,9 +600,6 @@ __device__ __forceinline__ void expand(const Params &p, const Tab<M> &t, Sh &sh,
         for (int r = 0; r < kChunks; r++) {
             const float t1 = cst[r] + __int_as_float(rec[r].z);
             cnd[r] = t1 - lv[r];
-            // (a placeholder is not offered: with an infinite bound it would
-            // claim a slot)
-            ok[r] = ok[r] && rec[r].z != kNoArc;
             key[r] = ok[r] ? okey(cnd[r]) : kEmptyKey;
             km = min(km, key[r]);
             d[r] = static_cast<uint32_t>(rec[r].x) & kDstMask;
@@ -614,7 +611,8 @@ __device__ __forceinline__ void expand(const Params &p, const Tab<M> &t, Sh &sh,
         // key may take its value now.
         km = wave_min_u32(km);
         if (km < cur && lane == 0) atomicMin(&c.best, km);
-        const uint32_t bnd = drop_bound(km < cur ? km : cur, p.beam);
+        // (never +inf: a placeholder would claim a slot)
+        const uint32_t bnd = min(drop_bound(km < cur ? km : cur, p.beam), kMaxKey);
 #pragma unroll
         for (int r = 0; r < kChunks; r++) act[r] = ok[r] && key[r] <= bnd;
         offer<M, kChunks, true>(p, t, sh, c, wq, act, d, de, cw, cnd, key);
