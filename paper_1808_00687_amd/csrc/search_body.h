@@ -37,7 +37,8 @@
 // set and the log-likelihood row (kSmall), one of twice the slots that takes
 // their place in LDS while the sets are too large for that copy (kBig; the
 // set and the row are then read from device memory), and one in device memory
-// (kDev).  A frame that reaches more states than its table holds is redone on
+// (kDev; the row and a larger copy of the set have the LDS to themselves).
+// A frame that reaches more states than its table holds is redone on
 // the next larger one.  Every table is private to its workgroup and there are
 // no per-frame launches; the only device-scope synchronisation is the
 // search's progress count, published every pub_k token sets when record
@@ -60,7 +61,9 @@
 // (about 1000 tokens): 14.5 -> 14.0 us (compaction 4.3 -> 1.9, the expansion
 // takes over part of its misses); about 20 tokens: 4.1 -> 3.3 us; frames of
 // about 4000 tokens, most of which the small table could not hold and redid in
-// device memory: 120 -> 92 us with the big LDS table.
+// device memory: 120 -> 92 us with the big LDS table; frames of about 7,200
+// tokens on the device-memory table: 264 -> 208 us with the row, the set and
+// its chunks in LDS (247 with the row and sets of up to 2944 tokens only).
 //
 // This header is compiled twice, once per translation unit:
 // search_kernel.hip instantiates the search alone, search_record_kernel.hip
@@ -88,7 +91,9 @@ constexpr int kBigBits = 14;
 constexpr int kBigSlots = 1 << kBigBits;  // slots of the big LDS table
 constexpr int kBigFill = 12800;           // states per frame it takes
 constexpr int kSetCache = 2496;           // tokens of the previous set kept in LDS for the expansion
+constexpr int kDevSet = 12160;            // the same beside the device-memory table
 constexpr int kCs = 512;                  // 64-arc chunks of the previous set described in LDS
+constexpr int kDevCs = 1024;              // the same beside the device-memory table
 constexpr int kQueue = 128;               // epsilon items per wave queue
 constexpr int kChunks = 2;                // 64-arc or 64-path chunks a wave has in flight (as pin() is called)
 constexpr int kMaxProbe = 64;             // linear-probe bound (the fill limit keeps probes short)
@@ -98,7 +103,7 @@ constexpr int kRowMax = 6144;             // log-likelihood columns a frame's LD
 constexpr uint32_t kClosureSizeMask = (1u << kClosureSizeBits) - 1u;
 
 static_assert(kHistBins <= 2 * kW * kQueue, "the select histogram aliases the epsilon queues");
-static_assert(kCs <= kW * kWave, "a wave's chunk descriptions fit its lanes");
+static_assert(kCs <= kDevCs && kDevCs <= kW * kWave, "a wave's chunk descriptions fit its lanes");
 
 // One frame's counters, two copies by frame parity.
 struct Cnt {
@@ -136,7 +141,8 @@ struct Prof {
     unsigned long long t_sub;
 };
 
-// What lies in LDS beside the small table, and with the big one.
+// What lies in LDS beside the small table, with the big one, and with the
+// device-memory table (the row in the same place as beside the small table).
 struct SmallLds {
     float row[kRowMax];            // the frame's log-likelihood row (L <= kRowMax)
     float2 cb[kSetCache];          // the last token set: cost, first emitting record - epre (as int)
@@ -149,6 +155,13 @@ struct SmallLds {
 struct BigLds {
     uint32_t keys[kBigSlots];
     uint32_t vals[kBigSlots];
+};
+
+struct DevLds {
+    float row[kRowMax];
+    float2 cb[kDevSet];
+    uint2 am[kDevCs];              // the chunk descriptions of a larger set
+    uint16_t cs[kDevCs];
 };
 
 struct Lds {
@@ -167,8 +180,28 @@ struct Lds {
     union {
         SmallLds s;
         BigLds b;
+        DevLds d;
     };
 };
+static_assert(offsetof(SmallLds, row) == offsetof(DevLds, row), "one place for the row");
+
+// Where the chunks are described beside table M, and how many.
+template <int M>
+__device__ __forceinline__ uint2 *chunk_am(Lds &lds)
+{
+    if constexpr (M == kDev) return lds.d.am;
+    else return lds.am;
+}
+
+template <int M>
+__device__ __forceinline__ uint16_t *chunk_cs(Lds &lds)
+{
+    if constexpr (M == kDev) return lds.d.cs;
+    else return lds.cs;
+}
+
+template <int M>
+constexpr int kChunksMax = M == kDev ? kDevCs : kCs;
 static_assert(sizeof(Lds) <= 160 * 1024, "the workgroup's LDS");
 
 // Fetch one word per active lane into LDS at `at` + 4 * lane without a
@@ -505,12 +538,12 @@ __device__ __forceinline__ int first_shift(uint32_t kb, uint32_t lim)
     return nb > kHistBits ? nb - kHistBits : 0;
 }
 
-// S_{k-1} for the expansion: in LDS beside the small table, else in device
-// memory.
+// S_{k-1} for the expansion: beside the small table in LDS, beside the
+// device-memory one in LDS if it fits there, else in device memory.
 struct SetView {
-    const float2 *cb;        // cost, first emitting record - epre (device memory: with the big table)
+    const float2 *cb;        // cost, first emitting record - epre
     const int32_t *epre;
-    const int32_t *state;    // device memory
+    const int32_t *state;    // device memory (a set without cb)
     const uint32_t *key;
     const uint16_t *cs;      // chunk descriptions
     uint2 *am;
@@ -530,27 +563,44 @@ __device__ __forceinline__ int window_owner(const int32_t *epre, int n, int a, i
     return min(t0 + owner_scan(pre, nx - pre, a0), n - 1);
 }
 
+// The same for a set in device memory: the cost of each lane's token and its
+// first emitting record - epre, the window's own loaded with its prefix (a
+// gather by owner would be a round trip more).
+__device__ __forceinline__ void window_token(const SetView &v, int a0, float &cst, int &rel)
+{
+    const int t0 = search_le(v.epre, v.n, a0);
+    const int i = min(t0 + lane_id(), v.n - 1);
+    const int pre = v.epre[i];
+    const int nx = i + 1 < v.n ? v.epre[i + 1] : v.a;
+    const int st = v.state[i];
+    const uint32_t key = v.key[i];
+    const bool in = t0 + lane_id() < v.n;
+    const int o = min(owner_scan(in ? pre : 0x7FFFFFFF, in ? nx - pre : 0, a0), v.n - 1 - t0);
+    cst = __shfl(okey_val(key), o, kWave);
+    rel = __shfl(st + 2 - pre, o, kWave);
+}
+
 // Emitting expansion of S_{k-1} into the table (step 1).  The frame's
-// log-likelihood row is read from LDS (srow) beside the small table when it
-// fits there, else from device memory (grow).
-template <int M>
+// log-likelihood row is read from LDS (srow) when it fits there, else, and with
+// the big table, from device memory (grow).  kCb: the set has v.cb.
+template <int M, bool kCb>
 __device__ __forceinline__ void expand(const Params &p, const Tab<M> &t, Sh &sh, Cnt &c, const SetView &v,
                                        const float *srow, const float *grow, WaveQ &wq)
 {
     const int lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const bool row_lds = M == kSmall && p.L <= kRowMax;
+    const bool row_lds = M != kBig && p.L <= kRowMax;
     const int nch = (v.a + kWave - 1) / kWave;
-    const bool described = M != kDev && nch <= kCs;
-    Chunks cd{0, 0u, 0u};
-    if constexpr (M != kDev) cd = take_chunks(v.cs, v.am, min(nch, kCs), wid, p.reverse != 0 && described);
+    const bool described = kCb && nch <= kChunksMax<M>;
+    const Chunks cd = take_chunks(v.cs, v.am, min(nch, kChunksMax<M>), wid, p.reverse != 0 && described);
     // wave w takes chunks w, w + kW, w + 2 kW, ... : every wave gets work
     int i = 0;   // chunks taken
     for (int c0 = wid; c0 < nch; c0 += kW * kChunks, i += kChunks) {
         // (this frame's cheapest candidate so far, and whether it is to be redone anyway)
         const uint32_t cur = c.best;
         if (__builtin_amdgcn_readfirstlane(c.overflow)) break;
-        int a[kChunks], tk[kChunks];
+        int a[kChunks], tk[kChunks], at[kChunks];
+        float cst[kChunks];
         bool ok[kChunks];
 #pragma unroll
         for (int r = 0; r < kChunks; r++) {
@@ -559,12 +609,15 @@ __device__ __forceinline__ void expand(const Params &p, const Tab<M> &t, Sh &sh,
             const int a0 = (p.reverse ? nch - 1 - ch : ch) * kWave;
             a[r] = a0 + lane;
             ok[r] = c0 + r * kW < nch && a[r] < v.a;
-            if (described) tk[r] = chunk_owner(cd, i + r);
-            else tk[r] = window_owner(v.epre, v.n, v.a, a0);
+            if constexpr (kCb) {
+                if (described) tk[r] = chunk_owner(cd, i + r);
+                else tk[r] = window_owner(v.epre, v.n, v.a, a0);
+            } else {
+                window_token(v, a0, cst[r], at[r]);
+                at[r] += a[r];
+            }
         }
-        float cst[kChunks];
-        int at[kChunks];
-        if constexpr (M != kDev) {
+        if constexpr (kCb) {
             float2 x[kChunks];
 #pragma unroll
             for (int r = 0; r < kChunks; r++) x[r] = v.cb[tk[r]];
@@ -572,12 +625,6 @@ __device__ __forceinline__ void expand(const Params &p, const Tab<M> &t, Sh &sh,
             for (int r = 0; r < kChunks; r++) {
                 cst[r] = x[r].x;
                 at[r] = __float_as_int(x[r].y) + a[r];
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < kChunks; r++) {
-                cst[r] = okey_val(v.key[tk[r]]);
-                at[r] = v.state[tk[r]] + 2 - v.epre[tk[r]] + a[r];
             }
         }
         int4 rec[kChunks];
@@ -844,9 +891,20 @@ __device__ __forceinline__ int frame(const Params &p, Lds &lds, const Tab<M> &t,
     } else {
         const float *grow = ll + static_cast<int64_t>(row_k) * p.L;
         const int64_t at = ly.sv0 + set.at;
-        const SetView v{M == kSmall ? lds.s.cb : gcb, M == kSmall ? lds.s.epre : p.sv_epre + at, p.sv_state + at,
-                        p.sv_key + at, lds.cs, lds.am, set.n, set.a};
-        expand<M>(p, t, sh, c, v, lds.s.row, grow, wq);
+        SetView v{nullptr, p.sv_epre + at, p.sv_state + at, p.sv_key + at, chunk_cs<M>(lds), chunk_am<M>(lds), set.n, set.a};
+        if constexpr (M == kSmall) {
+            v.cb = lds.s.cb;
+            v.epre = lds.s.epre;
+            expand<M, true>(p, t, sh, c, v, lds.s.row, grow, wq);
+        } else if constexpr (M == kBig) {
+            v.cb = gcb;
+            expand<M, true>(p, t, sh, c, v, lds.s.row, grow, wq);
+        } else if (set.n <= kDevSet) {
+            v.cb = lds.d.cb;
+            expand<M, true>(p, t, sh, c, v, lds.d.row, grow, wq);
+        } else {
+            expand<M, false>(p, t, sh, c, v, lds.d.row, grow, wq);
+        }
     }
     sub_close(p, pf, 4);
     // ---- 2. epsilon closure: each wave its own queue, then spill rounds ----
@@ -857,7 +915,7 @@ __device__ __forceinline__ int frame(const Params &p, Lds &lds, const Tab<M> &t,
     if (tid == kT - 2 * kWave) sh.c[(k + 1) & 1] = empty_cnt();
     // the next frame's log-likelihood row into LDS, where this frame's is no
     // longer read; the compaction's barrier waits for it
-    if (M == kSmall && p.L <= kRowMax && k < Tp) {
+    if (M != kBig && p.L <= kRowMax && k < Tp) {
         const float *nrow = ll + static_cast<int64_t>(row_next) * p.L;
         for (int i0 = wid * kWave; i0 < p.L; i0 += kT)
             fetch_lds(nrow + min(i0 + lane, p.L - 1), static_cast<uint32_t>(offsetof(Lds, s.row)) + 4 * i0);
@@ -994,7 +1052,8 @@ __device__ __forceinline__ int frame(const Params &p, Lds &lds, const Tab<M> &t,
             p.sv_epre[o] = apos;
             if (M == kBig && pos < kBigFill) gcb[pos] = make_float2(okey_val(vv), __int_as_float(dd + 2 - apos));
         }
-        if constexpr (M != kDev) mark_begin(lds.cs, lds.am, kCs, apos, deg, pos);
+        if (M == kDev && pos < kDevSet) lds.d.cb[pos] = make_float2(okey_val(vv), __int_as_float(dd + 2 - apos));
+        mark_begin(chunk_cs<M>(lds), chunk_am<M>(lds), kChunksMax<M>, apos, deg, pos);
     }
     {
         const int tx = wave_incl_scan(xacc), tz = wave_incl_scan(zacc);
@@ -1240,26 +1299,30 @@ __global__ __launch_bounds__(kT) void search_kernel(Params p)
                     const int words = 2 * (want == kBig ? kBigSlots : kSlots);
                     for (int i = tid; i < words; i += kT) keys[i] = kEmptyKey;
                     if (want == kBig) dev_clean = false;
-                    for (int i = tid; i < kCs; i += kT) lds.am[i] = make_uint2(0u, 0u);
-                    __syncthreads();
-                    // the set where this table's frames read it, and its chunks
-                    for (int i = tid; i < set.n; i += kT) {
-                        const int64_t o = ly.sv0 + set.at + i;
-                        const int32_t ep = p.sv_epre[o];
-                        const float2 x =
-                            make_float2(okey_val(p.sv_key[o]), __int_as_float(p.sv_state[o] + 2 - ep));
-                        if (want == kBig) {
-                            gcb[i] = x;
-                        } else {
-                            lds.s.cb[i] = x;
-                            lds.s.epre[i] = ep;
-                        }
-                        mark_begin(lds.cs, lds.am, kCs, ep, (i + 1 < set.n ? p.sv_epre[o + 1] : set.a) - ep, i);
-                    }
-                    if (want == kSmall && p.L <= kRowMax)
-                        for (int i = tid; i < p.L; i += kT)
-                            lds.s.row[i] = ldg(ll + static_cast<int64_t>(row_k) * p.L + i);
                 }
+                uint2 *am = want == kDev ? lds.d.am : lds.am;
+                uint16_t *cs = want == kDev ? lds.d.cs : lds.cs;
+                const int nch = want == kDev ? kDevCs : kCs;
+                for (int i = tid; i < nch; i += kT) am[i] = make_uint2(0u, 0u);
+                __syncthreads();
+                // the set where this table's frames read it, its chunks, and the row
+                for (int i = tid; i < set.n; i += kT) {
+                    const int64_t o = ly.sv0 + set.at + i;
+                    const int32_t ep = p.sv_epre[o];
+                    const float2 x = make_float2(okey_val(p.sv_key[o]), __int_as_float(p.sv_state[o] + 2 - ep));
+                    if (want == kBig) {
+                        gcb[i] = x;
+                    } else if (want == kSmall) {
+                        lds.s.cb[i] = x;
+                        lds.s.epre[i] = ep;
+                    } else if (i < kDevSet) {
+                        lds.d.cb[i] = x;
+                    }
+                    mark_begin(cs, am, nch, ep, (i + 1 < set.n ? p.sv_epre[o + 1] : set.a) - ep, i);
+                }
+                if (want != kBig && k > 0 && p.L <= kRowMax)
+                    for (int i = tid; i < p.L; i += kT)
+                        lds.s.row[i] = ldg(ll + static_cast<int64_t>(row_k) * p.L + i);
                 block_sync_vm();
                 mode = want;
             }
