@@ -184,6 +184,9 @@ struct Lds {
     };
 };
 static_assert(offsetof(SmallLds, row) == offsetof(DevLds, row), "one place for the row");
+// (a fetch's LDS address has 16 bits; the kernel's Lds lies at 0 unless it
+// gets another shared variable, which would be small)
+static_assert(offsetof(Lds, s.row) + sizeof(SmallLds::row) <= 63 * 1024, "a row fetch reaches the whole row");
 
 // Where the chunks are described beside table M, and how many.
 template <int M>
@@ -204,12 +207,14 @@ template <int M>
 constexpr int kChunksMax = M == kDev ? kDevCs : kCs;
 static_assert(sizeof(Lds) <= 160 * 1024, "the workgroup's LDS");
 
-// Fetch one word per active lane into LDS at `at` + 4 * lane without a
-// register or a wait: to bring its cache line near (into Sh::sink, which
-// nobody reads), or with a later fetch_wait and barrier to fill an array.
-// (m0, the fetch's LDS address, is put back: it is the compiler's.)
-__device__ __forceinline__ void fetch_lds(const void *ptr, uint32_t at)
+// Fetch one word per active lane into LDS at `to` + 4 * lane (the same `to` in
+// every lane) without a register or a wait: to bring its cache line near (into
+// Sh::sink, which nobody reads), or with a later fetch_wait and barrier to fill
+// an array.  (m0, the fetch's LDS address, is put back: it is the compiler's.)
+__device__ __forceinline__ void fetch_lds(const void *ptr, const void *to)
 {
+    // (the low half of a pointer to LDS is the LDS address)
+    const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(to));
     uint32_t keep;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
                  : "=&s"(keep)
@@ -477,7 +482,7 @@ __device__ __forceinline__ void offer(const Params &p, const Tab<M> &t, Sh &sh, 
         if (lane == 0) b = atomicAdd(&c.nslots, nc);
 #pragma unroll
         for (int r = 0; r < R; r++)
-            if (p.ahead && claimed[r]) fetch_lds(p.g.srec + d[r], static_cast<uint32_t>(offsetof(Lds, sh.sink)));
+            if (p.ahead && claimed[r]) fetch_lds(p.g.srec + d[r], sh.sink);
         b = __builtin_amdgcn_readlane(b, 0);
 #pragma unroll
         for (int r = 0; r < R; r++) {
@@ -918,7 +923,7 @@ __device__ __forceinline__ int frame(const Params &p, Lds &lds, const Tab<M> &t,
     if (M != kBig && p.L <= kRowMax && k < Tp) {
         const float *nrow = ll + static_cast<int64_t>(row_next) * p.L;
         for (int i0 = wid * kWave; i0 < p.L; i0 += kT)
-            fetch_lds(nrow + min(i0 + lane, p.L - 1), static_cast<uint32_t>(offsetof(Lds, s.row)) + 4 * i0);
+            fetch_lds(nrow + min(i0 + lane, p.L - 1), lds.s.row + i0);
     }
     if (c.spill_n[0] && !c.overflow && !sh.status) {
         // spilled items are read by other waves
