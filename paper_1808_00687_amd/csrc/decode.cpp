@@ -535,9 +535,12 @@ constexpr int kRecPublish = 16;
 // Up to this many utterances the search fetches the lines of the states it
 // claims ahead of their use: they have arrived when the compaction reads them.
 // Few searches leave the memory idle; with many the fetches for states that do
-// not survive cost more than the wait.  Measured with / without: one utterance
-// 17.1 / 17.6 ms, 64 30.3 / 29.6, 256 63.1 / 59.7.
-constexpr int kAheadUtts = 32;
+// not survive cost more than the wait.  The line lies below the smallest batch
+// that is split into length groups.  Measured on the 25M-arc graph, utterances
+// of 300-500 frames, best path, without / with: one 3.69 / 3.56 ms, 4 5.98 /
+// 5.86, 16 8.44 / 8.21, 24 9.20 / 9.05, 31 9.49 / 9.36; 32 8.70 / 8.78, 40
+// 8.86 / 8.94, 48 9.04 / 9.09, 64 9.56 / 9.76, 96 11.43 / 11.80.
+constexpr int kAheadUtts = 31;
 // The lattice regions with the incremental pass: this fraction of the
 // one-shot regions (the pass keeps a few percent of the raw arcs; an
 // overflow grows every buffer and decodes again)
