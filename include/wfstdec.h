@@ -70,7 +70,9 @@ typedef struct wfst_result wfst_result;
  *                invalid (the end node E of Alg. 1 as final costs)
  *   out          receives the graph handle
  *
- * The epsilon subgraph must be acyclic.  Input arrays are copied and may be
+ * The epsilon subgraph must be acyclic.  The device layout must have fewer
+ * than 2^31 units of 16 bytes: two a state, one an emitting arc, and one for
+ * each state without emitting arcs.  Input arrays are copied and may be
  * freed on return.  The handle is immutable and may be shared by concurrent
  * decodes on different streams of the same device.  Errors: WFST_EINVAL
  * (any rule above), WFST_ENOMEM, WFST_EDEVICE.
@@ -278,8 +280,8 @@ typedef struct wfst_stats {
        queues, [1] closure rounds over spilled epsilon items, [2] beam and
        max-active pruning, [3] compaction of the survivors (which also clears
        the token table); [4] the emitting expansion as the first wave sees it
-       (part of [0]); [5] between frames (bookkeeping and the frame's first
-       barrier); [6] frames abandoned for the device-memory table (their
+       (part of [0]); [5] between frames (bookkeeping, the switch to another
+       token table); [6] frames abandoned for a larger token table (their
        steps are not in [0]-[3]) */
     double search_phase_ms[7];
     /* with WFST_PROFILE_STEPS: this utterance's backtrace and lattice-beam pruning,
@@ -420,14 +422,15 @@ int wfst_decode_noalloc(const wfst_graph *g, const float *loglikes, int32_t T, i
  * field keeps the library's default; a positive fill or capacity is used only
  * when it is below the default.
  *
- *   lds_fill           states per frame the search's LDS token table takes
- *                      before the frame is redone with the table in device
- *                      memory
+ *   lds_fill           states per frame either of the search's LDS token
+ *                      tables takes before the frame is redone on the next
+ *                      larger one (small LDS table, big LDS table, device
+ *                      memory)
  *   queue_cap          epsilon items per wave queue in LDS before items spill
  *                      to device memory
  *   record_fill        survivors per token set that the record pass handles
- *                      with its LDS table (larger sets go to the large-set
- *                      pass)
+ *                      with either of its LDS tables (larger sets go to the
+ *                      large-set pass)
  *   record_big_fill    the same for the large-set pass (larger sets use a
  *                      device-memory table)
  *   lattice_lds        survivors per token set that lattice pruning keeps in

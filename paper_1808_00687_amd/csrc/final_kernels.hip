@@ -1195,10 +1195,16 @@ __device__ void lattice_block(const Params &p, int u, uint32_t *s_e, float *s_c,
 // it, as the set behind the chunk does; the last set's epsilon records are
 // left whole too.
 //
-// Which utterances: a block's own chain is 2-3 us a set, so shorter ones wait
-// longer for the chunks than their backward pass gains (one of 82 frames:
-// 0.71 ms without, 0.77 with; one of 336: 0.916 and 0.952), and small raw sets
-// cost the backward pass little.  Shorter chunks leave more records (64
+// Which utterances: a block's own chain is 2-3 us a set, so a short one may wait
+// longer for the chunks than its backward pass gains, and small raw sets cost
+// that pass little.  From 512 frames on it gained wherever it was measured
+// (whole decode without / with: one utterance of about 1100 tokens a set, 512
+// frames 7.54 / 7.15 ms, 800 11.88 / 11.18; of about 4500, 512 55.8 / 54.1, 800
+// 81.1 / 79.3).  Below it depends on the sets: gains from 200 frames on at 1100
+// tokens (2.71 / 2.64, 336 frames 4.85 / 4.65), none at 128 frames of 4300
+// (14.59 / 14.64), losses at about 145 (336 frames 0.916 / 0.952) and at 82
+// frames (0.71 / 0.77).  The line is on the safe side of all of them, not where
+// each breaks even.  Shorter chunks leave more records (64
 // utterances: 29.9 ms with 16 sets, 29.35 with 32).  Tables of 4096 survivors
 // and half the waves let four blocks share a CU, which counts where the blocks
 // are many (256 utterances: 48.7 ms, 49.5 with 8192); a launch of few blocks

@@ -1,22 +1,21 @@
 // Internal structures of the wfstdec HIP library (gfx950).
 //
-// Device layout of a graph (built once by wfst_load):
-//   eoff[N+1]  emitting-arc row offsets; earc[] 16-byte records
-//              {dst | has_eps << 31, column = ilabel - 1, weight bits, user arc}
-//   xoff[N+1]  epsilon-arc row offsets; xarc[] 16-byte records
-//              {dst | has_eps << 31, weight bits, user arc, 0}
+// Device layout of a graph (built once by wfst_load; the words of each record
+// are at DevGraph):
+//   node[]     16-byte units: each state's two records (its rows and a copy of
+//              its first epsilon record with the place of its epsilon-closure
+//              list), then its emitting arcs.  A state is known on the device
+//              by the unit of its first record; one load gives its rows, the
+//              next word the epsilon arc of the common single-epsilon state
+//   eua[]      user arc of each emitting arc, by its unit in node
+//   xarc[]     epsilon arcs by source, 16 bytes each
 //   arc_src[E] user arc -> src state | is_epsilon << 31 (cold, back-pointers)
-//   final_w[N] final costs or null
-//   srec[2N]   32-byte state records: the state's emitting and epsilon row
-//              offsets, then a copy of its first epsilon record (zeros if
-//              none), so that one load gives a state's rows and, for the
-//              common single-epsilon state, its epsilon arc; the copy's last
-//              word locates the state's epsilon-closure list
+//   final_w    final costs by device id, or null
 //   ctab[]     epsilon-closure lists: every epsilon path from a state (up to
-//              size and length limits) as {last destination, last arc,
-//              length, the weights along the path} in three 16-byte words,
-//              so the closure from a lowered token needs no chain of
-//              dependent loads
+//              size and length limits) as {last destination, the weights along
+//              the path, length} in three 16-byte words, so the closure from a
+//              lowered token needs no chain of dependent loads
+//   uarc[E]    user arc -> its output label and record
 // Each state's arcs keep their user order inside the emitting and the
 // epsilon partition.  has_eps marks a destination with epsilon out-arcs, so a
 // kernel that lowers its token knows without another load whether the
@@ -135,7 +134,7 @@ struct UttState {
     int32_t T;
     int32_t Tp;           // decoded frames (set by the classify kernel)
     int32_t status;       // WFST_OK, WFST_ENOPATH or WFST_ECAPACITY
-    int32_t gframes;      // frames whose token table overflowed LDS (redone in device memory)
+    int32_t gframes;      // frames on the device-memory token table
     // written by the search kernel when it ends
     int32_t n_last;       // |S_T'|
     int32_t big_sets;     // kSetMid, kSetLarge: some token set is too large for the record kernel's small table, for any
@@ -181,10 +180,10 @@ struct Params {
     int32_t n_blank;
     int32_t frame_stride;       // >= 1
     float blank_thr;
-    int32_t lds_fill;         // states per frame the LDS token table takes (<= its fill limit)
+    int32_t lds_fill;         // states per frame either LDS token table takes (<= its fill limit)
     int32_t gen_lds;          // epsilon pool entries in LDS (<= its capacity)
     int32_t profile;          // count device clock ticks per search step
-    int32_t rec_fill;         // survivors per set the record kernel's LDS table takes (<= its fill limit)
+    int32_t rec_fill;         // survivors per set either LDS table of the record kernel takes (<= its fill limit)
     int32_t rec_big_fill;     // the same for the large-set pass's LDS table
     int32_t lat_lds;          // survivors per set the lattice backward pass keeps in LDS (<= its capacity)
     uint32_t hash_mul;        // state hash multiplier of the token tables
@@ -205,14 +204,14 @@ struct Params {
     int32_t *rvals;
     UttState *st;
     const UttLayout *lay;
-    // survivors (per utterance regions); the search writes state, cost key,
-    // first emitting record and emitting prefix, the record pass the
-    // back-pointer (source survivor and user arc)
+    // survivors (per utterance regions); the search writes state, cost key
+    // and emitting prefix, the record pass the back-pointer (source survivor
+    // and user arc)
     int32_t *sv_state;
     uint32_t *sv_key;         // ordered key of the token cost
     int32_t *sv_prev;         // survivor the back-pointer arc leaves from (-1 for the start token)
     int32_t *sv_arc;          // back-pointer user arc (-1 for the start token)
-    int32_t *sv_epre;         // exclusive prefix of emitting out-degree within the token set
+    int32_t *sv_epre;         // exclusive prefix of emitting records (placeholders too) within the token set
     unsigned long long *sv_win;   // record pass scratch for sets beyond its LDS table:
                                   // (user arc + 1) << 32 | source survivor of the winning arc
     uint32_t *e_key;          // lattice backward extra cost per survivor (ordered key)
@@ -240,7 +239,8 @@ struct Params {
     int32_t *path_frame;
     int2 *path_packed;        // every utterance's path {arc, frame}, one after another
     // search scratch per utterance: token table in device memory (frames that
-    // overflow LDS), epsilon item spill lists, emitting candidate lists
+    // overflow the LDS ones; beside the big LDS table gkeys and gvals hold the
+    // last set's costs and records, gslots its slot list), epsilon item spill lists
     uint32_t *gkeys;          // U x capG
     uint32_t *gvals;
     int32_t *gslots;
