@@ -44,3 +44,10 @@ def test_record_table_edges(dec, torch_mod, oracle_mod, n, cols, frames):  # noq
     ll[np.arange(frames), at[kind]] = rng.integers(-3, 4, size=frames)
     ro, rg = both(dec, torch_mod, oracle_mod, g, ll, beam=50.0, lattice_beam=4.0)
     parity.assert_same(ro, rg, lattice=True, tag="%d survivors, %d columns, %d frames" % (n, cols, frames))
+
+
+@pytest.mark.parametrize("n,cols,frames", [(3072, 4096, 2048), (3071, 4095, 2056), (6145, 4096, 2048)])
+def test_record_table_edges_two_launches(dec, torch_mod, oracle_mod, n, cols, frames):  # noqa: F811
+    # more than 2048 sets: the small table at its limit with the row in LDS,
+    # and a set beyond the middle table's limit
+    test_record_table_edges(dec, torch_mod, oracle_mod, n, cols, frames)
